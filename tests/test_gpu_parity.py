@@ -250,6 +250,62 @@ def test_prefill_attention_over_packed_cache(case):
     assert worst <= 2e-3
 
 
+@pytest.mark.parametrize("k_budget,v_bits,G,n_kv,n_q,pos0,dtype", [
+    (64, 1, 1, 1, 70, [0], "bf16"), (96, 3, 3, 2, 131, [61, 7], "fp32"), (448, 5, 5, 1, 33, [100], "bf16"),
+    (512, 8, 8, 1, 17, [64], "fp32"), (224, 7, 6, 2, 65, [1, 190], "bf16"), (320, 6, 2, 1, 129, [0], "bf16"),
+    (256, 4, 7, 2, 200, [3], "fp32"), (160, 2, 8, 8, 530, [40, 0], "bf16")])
+def test_prefill_attention_tile_edges(k_budget, v_bits, G, n_kv, n_q, pos0, dtype):
+    """Causal prefill attention where a tile, a workgroup or a packed row ends:
+    every value width, key rows of 4 to 32 words with codes up to 8 bits (looked
+    up in pairs up to 6), G = 1 to 8, single-row tails, start positions on and
+    off a tile, and both workgroup shapes (the last case has more than 256
+    workgroups of 128 rows).  Every head at the positions around the tile and
+    workgroup edges, against the oracle within 2e-3.  A head in which a
+    coordinate lies within rounding of a decision threshold (the tie bound of
+    compare_codes) may hold another code there, which moves its logits by a
+    whole quantization step: its attention is not compared (at most one head in
+    eight)."""
+    bg = bgm()
+    total = [p + n_q for p in pos0]
+    T, B = max(total), len(pos0)
+    st = P.make_setup(60 + v_bits, 1, B, n_kv, G, (T + 63) // 64 * 64, k_budget, v_bits, 5e5, dtype)
+    layout, cache = build(st)
+    kv = {(b, h): P.keys_values(st, 0, h, 2000 * b, T) for b in range(B) for h in range(n_kv)}
+    append(st, layout, cache, 0, [[kv[b, h] for h in range(n_kv)] for b in range(B)], [0] * B)
+    rng = np.random.default_rng(k_budget)
+    q = synth.cast(rng.standard_normal((B, n_q, n_kv * G, 128)), dtype)
+    log("prefill edges", k_budget, v_bits, G, n_q, pos0)
+    out = bg.blockgtq_prefill_attn(st.cfg, layout, 0, to_dev(q, dtype),
+                                   torch.tensor(pos0, dtype=torch.int32, device="cuda"), T - 1, cache)
+    out = out.cpu().numpy().astype(np.float64)
+    worst, stats, tied = 0.0, P.Stats(), 0
+    for b in range(B):
+        rows_per = max(1, 128 // G)
+        want = {0, 1, n_q - 1, n_q // 2} | {e + d for e in range(rows_per, n_q, 4 * rows_per) for d in (-1, 0, 1)}
+        want |= {64 * m - pos0[b] + d for m in (1, 2, 5) for d in (-1, 0)}
+        at = np.array(sorted(i for i in want if 0 <= i < n_q))
+        for h in range(n_kv):
+            rows = P.oracle_rows(st, 0, h, kv[b, h][0], kv[b, h][1])
+            before = stats.code_ties
+            widths = P.stream_widths(st.bits[0, h])
+            kw = cache.k_codes[0, b, h, :T].cpu().numpy().view(np.uint32)
+            P.compare_codes(P.read_fields(kw, widths), rows.kcodes, rows.kz, widths, P.group_dims(st.bits[0, h]), stats)
+            vw = cache.v_codes[0, b, h].cpu().numpy().view(np.uint32)
+            P.compare_codes(P.read_value_codes(vw, v_bits, T), rows.vcodes, rows.vz, [v_bits] * 128,
+                            np.full(128, 128), stats)
+            if stats.code_ties > before:
+                tied += 1
+                continue
+            kh = o.dequantize_keys(rows.kcodes, rows.knorms, st.bits_oracle[0, h], st.rot_k)
+            vh = o.dequantize_values(rows.vcodes, rows.vnorms, st.rot_v, v_bits)
+            qq = q[b, at, h * G:(h + 1) * G].reshape(-1, 128)
+            ref = o.prefill_attention(qq, np.repeat(pos0[b] + at, G), kh, vh)
+            worst = max(worst, P.rel_err(out[b, at, h * G:(h + 1) * G].reshape(-1, 128), ref))
+    log("prefill edges max rel err", worst, "tied heads", tied)
+    assert worst <= 2e-3
+    assert tied <= max(1, B * n_kv // 8)
+
+
 def test_uniform_k2_decode_many_positions():
     """Decode over a uniform K2 layout (one 2-bit group holding the whole
     key), the layout where the dropped lo part of the query matters most:
