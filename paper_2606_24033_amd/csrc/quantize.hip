@@ -32,13 +32,11 @@
 
 #include "kernels.h"
 #include "layout.h"
-#include "split.h"
 
 namespace bgtq {
 namespace quant_detail {
 
-using namespace split;
-
+typedef float float4_t __attribute__((ext_vector_type(4)));
 
 // Workgroups of W waves: 16 for long appends (the 64 KB matrix staged in LDS
 // serves more rows), 4 for calls of up to 64K rows, which then spread over
@@ -47,6 +45,8 @@ using namespace split;
 // tiles keeps each SIMD's MFMA pipe busy ~30 us on its own, with most CUs
 // idle in a short call.)
 constexpr int kWavesLong = 16, kWavesShort = 4;
+constexpr int kSub = 16;                          // rows per wave sub-tile (one MFMA column block)
+constexpr int kMatF4 = kMfmaMatFloats / 4;        // float4 entries of one MFMA-order matrix
 
 template <int W>
 struct LdsK {
@@ -523,12 +523,16 @@ __global__ __launch_bounds__(W * 64) void k_quant_rows(Dims d, const uint8_t* __
 
 // ---------------------------------------------------------------- bf16 inputs
 // bf16 rows of the ordinary widths (key rows of up to kSplitKWords words,
-// values of up to kSplitVBits bits) on three exact bf16 products (split.h).
-// The group radii stay on fp32 MFMAs (their squares don't fit bf16).
-// 131072 rows x 8 heads, K2V2: 809 us with fp32 products, 303 us here; 8192
-// rows x 2 heads, K3V3: 23.7 and 17.3 us.  fp32 inputs, and the wider formats
-// (whose packing buffers don't fit beside 96 KB of matrix), keep the fp32
-// products.
+// values of up to kSplitVBits bits).  An fp32 matrix entry is the exact sum of
+// three bf16 numbers (8 + 8 + 8 bits of its significand, taken by truncation)
+// and a bf16 input is an operand as it lies in memory, so the 128 x 128
+// products run as three v_mfma_f32_16x16x32_bf16 products whose terms are
+// exact in fp32: the only rounding left is that of the fp32 accumulation.
+// The three cost 3/16 of the fp32 matrix time.  The group radii stay on fp32
+// MFMAs (their squares don't fit bf16).  131072 rows x 8 heads, K2V2: 809 us
+// with fp32 products, 334 us here; 8192 rows x 2 heads, K3V3: 23.7 and
+// 21.7 us.  fp32 inputs, and the wider formats (whose packing buffers don't
+// fit beside 96 KB of matrix), keep the fp32 products.
 //
 // A wave takes 32 rows at a time, so that each matrix operand read from LDS
 // (96 KB per workgroup, split while it is staged) serves two products, and
@@ -536,13 +540,17 @@ __global__ __launch_bounds__(W * 64) void k_quant_rows(Dims d, const uint8_t* __
 // 16 accumulator registers, so four waves fit a SIMD.  Codes by counting: up
 // to three (width <= 2) or seven (width 3) comparisons against thresholds
 // held per position, binary search only for tiles that hold wider codes.
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef uint32_t uint4_t __attribute__((ext_vector_type(4)));
 constexpr int kSplitKWords = 16, kSplitVBits = 4;
+constexpr int kSplitRows = 2 * kSub;        // rows of a wave
+constexpr int kMatOps = kMatF4 / 2;         // 8-element operands of one matrix: [t][q][lane]
 
 template <int W>
 struct LdsKS {
   uint4_t wa[3][kMatOps];                        // W's three parts, A operand order
   float4 ma[8 * 64];                             // group membership, fp32 A operand order
-  float4 ta[kHeadDim], tb[kHeadDim];             // first seven thresholds of each position, NaN past its last
+  float4 ta[kHeadDim], tb[kHeadDim];             // first seven thresholds of each position, +inf past its last
   uint32_t rw[W][kSplitRows * kSplitKWords];     // per wave: packed key rows, k_words apart
   float sc[W][kSplitRows][kMaxGroups];           // per wave: sqrt(d_g) / radius
   uint32_t pm[kHeadDim];                         // bit offset | b << 10 | group << 14
@@ -559,6 +567,82 @@ struct LdsVSplit {
   float thr[kThresholdEntries];
 };
 static_assert(sizeof(LdsKS<kWavesLong>) <= 160 * 1024 && sizeof(LdsVSplit<kWavesLong>) <= 160 * 1024, "LDS");
+
+__device__ __forceinline__ float4_t mfma_bf16(uint4_t a, uint4_t b, float4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c,
+                                                 0, 0, 0);
+}
+
+// The fp32 matrix from memory into its three bf16 parts in LDS: operand o =
+// (t * 4 + q) * 64 + lane holds the lane's input dims 32 (lane / 16) + 8 q ..
+// + 7, two float4 of the fp32 order.
+template <int W>
+__device__ __forceinline__ void stage_split(uint4_t (*dst)[kMatOps], const float4* __restrict__ src, int tid) {
+  constexpr int kPer = kMatOps / (W * 64), kRound = kPer < 4 ? kPer : 4;
+  static_assert(kMatOps % (W * 64) == 0 && kPer % kRound == 0, "matrix staging");
+#pragma unroll 1
+  for (int u0 = 0; u0 < kPer; u0 += kRound) {
+    float4 lo[kRound], hi[kRound];
+#pragma unroll
+    for (int u = 0; u < kRound; ++u) {
+      const int o = tid + (u0 + u) * W * 64, f = ((o >> 6) * 2) * 64 + (o & 63);
+      lo[u] = src[f];
+      hi[u] = src[f + 64];
+    }
+#pragma unroll
+    for (int u = 0; u < kRound; ++u) {
+      const float w[8] = {lo[u].x, lo[u].y, lo[u].z, lo[u].w, hi[u].x, hi[u].y, hi[u].z, hi[u].w};
+      uint32_t part[3][8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        part[0][e] = __float_as_uint(w[e]) & 0xFFFF0000u;
+        const float r1 = w[e] - __uint_as_float(part[0][e]);
+        part[1][e] = __float_as_uint(r1) & 0xFFFF0000u;
+        part[2][e] = __float_as_uint(r1 - __uint_as_float(part[1][e]));
+      }
+#pragma unroll
+      for (int p = 0; p < 3; ++p) {
+        uint4_t v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = (part[p][2 * e] >> 16) | (part[p][2 * e + 1] & 0xFFFF0000u);
+        dst[p][tid + (u0 + u) * W * 64] = v;
+      }
+    }
+  }
+}
+
+// The lane's 32 dims of one bf16 row as four operands.
+__device__ __forceinline__ void load_operands(const void* src, size_t elem_off, bool valid, uint4_t (&x)[4]) {
+  const uint4_t* p = reinterpret_cast<const uint4_t*>(static_cast<const uint16_t*>(src) + elem_off);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) x[q] = valid ? p[q] : uint4_t{0u, 0u, 0u, 0u};
+}
+
+__device__ __forceinline__ float bf16_elem(const uint4_t (&x)[4], int i) {  // i known at compile time
+  const uint32_t w = x[i >> 3][(i & 7) >> 1];
+  return __uint_as_float(i & 1 ? w & 0xFFFF0000u : w << 16);
+}
+
+// Output tile t of the products of the wave's two sub-tiles (KEYS: the matrix
+// is the A operand).  The two small parts have their own accumulator.
+template <bool KEYS>
+__device__ __forceinline__ void split_product(const uint4_t (*mat)[kMatOps], int t, int lane, const uint4_t (&x)[2][4],
+                                              float4_t (&out)[2]) {
+  float4_t hi[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}}, lo[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int o = (t * 4 + q) * 64 + lane;
+    const uint4_t w0 = mat[0][o], w1 = mat[1][o], w2 = mat[2][o];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) lo[s] = KEYS ? mfma_bf16(w2, x[s][q], lo[s]) : mfma_bf16(x[s][q], w2, lo[s]);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) hi[s] = KEYS ? mfma_bf16(w0, x[s][q], hi[s]) : mfma_bf16(x[s][q], w0, hi[s]);
+#pragma unroll
+    for (int s = 0; s < 2; ++s) lo[s] = KEYS ? mfma_bf16(w1, x[s][q], lo[s]) : mfma_bf16(x[s][q], w1, lo[s]);
+  }
+#pragma unroll
+  for (int s = 0; s < 2; ++s) out[s] = hi[s] + lo[s];
+}
 
 template <int W>
 __device__ __forceinline__ void quant_keys_split(LdsKS<W>& S, int bx, int iters, const Dims& d,
@@ -590,7 +674,7 @@ __device__ __forceinline__ void quant_keys_split(LdsKS<W>& S, int bx, int iters,
                 (static_cast<uint32_t>(g) << 14);
     float th[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) th[j] = j < n ? gthr[thr_index(b) + j] : __builtin_nanf("");
+    for (int j = 0; j < 8; ++j) th[j] = j < n ? gthr[thr_index(b) + j] : __builtin_huge_valf();
     S.ta[tid] = make_float4(th[0], th[1], th[2], th[3]);
     S.tb[tid] = make_float4(th[4], th[5], th[6], th[7]);
   }
@@ -605,17 +689,13 @@ __device__ __forceinline__ void quant_keys_split(LdsKS<W>& S, int bx, int iters,
                  tid);
   __syncthreads();
   for (int i = tid; i < 8 * 64; i += kThreads) {
-    // row 4 m + e of the product is group 2 m + e (e < 2): two groups to each
-    // quarter of the wave instead of four to two of them
-    const int s4 = i >> 6, l = i & 63, d0 = 32 * (l >> 4) + 4 * s4;
-    const int g = (l & 3) < 2 ? 2 * ((l >> 2) & 3) + (l & 3) : -1;
+    const int s4 = i >> 6, l = i & 63, g = l & 15, d0 = 32 * (l >> 4) + 4 * s4;
     S.ma[i] = make_float4(S.gd[d0] == g ? 1.f : 0.f, S.gd[d0 + 1] == g ? 1.f : 0.f, S.gd[d0 + 2] == g ? 1.f : 0.f,
                           S.gd[d0 + 3] == g ? 1.f : 0.f);
   }
   __syncthreads();
 
   const int tk = lane & 15, kk = lane >> 4;
-  const float gs[2] = {S.gs[2 * kk], S.gs[2 * kk + 1]};
   const int nslot = (ng + 1) & ~1;
   const size_t row = (static_cast<size_t>(layer) * d.batch + seq) * d.n_kv + head;
   for (int it = 0; it < iters; ++it) {
@@ -642,25 +722,20 @@ __device__ __forceinline__ void quant_keys_split(LdsKS<W>& S, int bx, int iters,
         }
       __builtin_amdgcn_sched_barrier(0);  // (eight steps' squares at once would spill)
     }
-    // this lane holds R2 of rows tk, 16 + tk for groups 2 kk, 2 kk + 1 (zero
-    // past the last group)
+    // this lane holds R2 of rows tk, 16 + tk for groups 4 kk .. 4 kk + 3
 #pragma unroll
-    for (int s = 0; s < 2; ++s) {
-      const int r = r0 + kSub * s + tk;
-      float nrm[2];
-      uint16_t h[2];
+    for (int s = 0; s < 2; ++s)
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        nrm[i] = sqrtf(n2[s][i]);
-        S.sc[wave][kSub * s + tk][2 * kk + i] = nrm[i] > 0.f ? gs[i] / nrm[i] : 0.f;
-        h[i] = __half_as_ushort(__float2half_rn(nrm[i]));
+      for (int i = 0; i < 4; ++i) {
+        const int g = 4 * kk + i, r = r0 + kSub * s + tk;
+        if (g < ng) {
+          const float nrm = sqrtf(n2[s][i]);
+          S.sc[wave][kSub * s + tk][g] = nrm > 0.f ? S.gs[g] / nrm : 0.f;
+          if (r < n_fit)
+            c.k_norms[row * kMaxGroups * cap + static_cast<size_t>(wp + r) * nslot + g] =
+                __half_as_ushort(__float2half_rn(nrm));
+        }
       }
-      if (r < n_fit && 2 * kk < ng) {
-        uint16_t* dst = c.k_norms + row * kMaxGroups * cap + static_cast<size_t>(wp + r) * nslot + 2 * kk;
-        if (2 * kk + 1 < ng) *reinterpret_cast<uint32_t*>(dst) = h[0] | static_cast<uint32_t>(h[1]) << 16;
-        else *dst = h[0];
-      }
-    }
     wave_sync();
     // Z[p][row] = sum_d W[p][d] x[row][d]; codes of stream positions
     // 16 t + 4 kk + i of a row: one bit field
@@ -697,30 +772,26 @@ __device__ __forceinline__ void quant_keys_split(LdsKS<W>& S, int bx, int iters,
                             (th.z <= z[s][i] ? 1u : 0u);
           }
         }
+        // a +inf past a narrow position's last threshold is no threshold
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int s = 0; s < 2; ++s) code[s][i] = min(code[s][i], (1u << ((pm[i] >> 10) & 15)) - 1u);
       } else {
 #pragma unroll
         for (int s = 0; s < 2; ++s)
 #pragma unroll
           for (int i = 0; i < 4; ++i) code[s][i] = 0u;
-        // all lanes read on every step (a narrow position's index stays inside
-        // the table: thr_index(7) + 127 at most) and the eight reads of a step
-        // are in flight together
 #pragma unroll 1
-        for (uint32_t step = 1u << (mw - 1); step > 0; step >>= 1) {
-          float tv[2][4];
+        for (uint32_t step = 1u << (mw - 1); step > 0; step >>= 1)
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            const int first = thr_index((pm[i] >> 10) & 15) + static_cast<int>(step) - 1;
+            const int b = (pm[i] >> 10) & 15;
+            const bool in = step < (1u << b);  // (thr_index(b) + step - 1 is inside the table for every b)
+            const float* th = S.thr + thr_index(b) + step - 1;
 #pragma unroll
-            for (int s = 0; s < 2; ++s) tv[s][i] = S.thr[first + static_cast<int>(code[s][i])];
+            for (int s = 0; s < 2; ++s) code[s][i] += in && th[code[s][i]] <= z[s][i] ? step : 0u;
           }
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const uint32_t add = (step >> ((pm[i] >> 10) & 15)) == 0 ? step : 0u;
-#pragma unroll
-            for (int s = 0; s < 2; ++s) code[s][i] += tv[s][i] <= z[s][i] ? add : 0u;
-          }
-        }
       }
       const int b0 = (pm[0] >> 10) & 15, b1 = b0 + ((pm[1] >> 10) & 15), b2 = b1 + ((pm[2] >> 10) & 15);
       const int nb = b2 + ((pm[3] >> 10) & 15), bo = pm[0] & 1023, w = bo >> 5, sh = bo & 31;
