@@ -464,49 +464,6 @@ def test_prefill_append_kernels_widths_and_offsets(k_budget, v_bits, dtype):
     assert stats.code_ties <= 1e-4 * stats.codes
 
 
-@pytest.mark.parametrize("n,n_kv,wp,k_budget,v_bits", [(66001, 1, 3, 128, 2), (20003, 5, 31, 192, 3),
-                                                       (131107, 5, 0, 64, 1), (16421, 4, 17, 256, 4)])
-def test_long_bf16_appends_match_fp32_products(n, n_kv, wp, k_budget, v_bits):
-    """bf16 rows (three exact bf16 parts of the matrix) against the fp32
-    products on the same numbers as fp32 inputs: long calls, whose last
-    workgroup, wave and value tile are partial, in one call, in short calls
-    (the other workgroup size) and in fp32.  One call and short calls sum in
-    the same order: equal bytes.  Against fp32 only a coordinate within
-    rounding of a threshold may differ (2e-7 of the codes in either sum, a
-    word holds up to 32 of them: 1e-5 of the words); radii equal.  Zero,
-    huge, infinite and NaN rows are among them."""
-    bg = bgm()
-    st = P.make_setup(70 + v_bits, 1, 1, n_kv, 4, (wp + n + 63) // 64 * 64, k_budget, v_bits, 5e5, "bf16")
-    g = torch.Generator(device="cuda").manual_seed(n)
-    sig = torch.exp(torch.randn(128, generator=g, device="cuda"))
-    K = (torch.randn((1, n, n_kv, 128), generator=g, device="cuda") * sig).bfloat16()
-    V = torch.randn((1, n, n_kv, 128), generator=g, device="cuda").bfloat16()
-    for x in (K, V):
-        x[:, 40] = 0
-        x[:, 41, :, 5] = 1e25
-        x[:, n - 3, :, 77] = float("inf")
-        x[:, n - 2, :, 126] = float("nan")
-
-    def quantize(dtype, chunk):
-        cfg = bg.Config(n_layers=1, batch=1, n_kv_heads=n_kv, group=4, capacity=st.cfg.capacity, k_budget=k_budget,
-                        v_bits=v_bits, in_dtype=bg.BGTQ_BF16 if dtype == torch.bfloat16 else bg.BGTQ_FP32)
-        layout = bg.Layout(cfg, st.bits, synth.flat_rot_k(st.rot_k), st.rot_v)
-        cache = bg.Cache(cfg)
-        for i in range(0, n, chunk):
-            at = torch.tensor([wp + i], dtype=torch.int32, device="cuda")
-            bg.blockgtq_quantize_append(cfg, layout, 0, K[:, i:i + chunk].to(dtype).contiguous(),
-                                        V[:, i:i + chunk].to(dtype).contiguous(), at, cache, host_write_pos=[wp + i])
-        return [t.view(torch.int32 if t.dtype in (torch.int32, torch.uint32) else torch.int16).clone()
-                for t in (cache.k_codes, cache.v_codes, cache.k_norms, cache.v_norms)]
-
-    one, short, ref = quantize(torch.bfloat16, n), quantize(torch.bfloat16, 12001), quantize(torch.float32, n)
-    for a, b in zip(one, short):
-        assert torch.equal(a, b)
-    for a, b in zip(one[:2], ref[:2]):
-        assert int((a != b).sum()) <= 2 + 1e-5 * a.numel()
-    assert torch.equal(one[2], ref[2]) and torch.equal(one[3], ref[3])
-
-
 def test_fp16_comparator_group8_ragged_and_poisoned_tail():
     """The fp16 comparator decode (MFMA kernel) with G = 8 query heads per KV
     head, ragged contexts that end inside a tile, several splits, and NaN in
