@@ -306,6 +306,32 @@ def test_prefill_attention_tile_edges(k_budget, v_bits, G, n_kv, n_q, pos0, dtyp
     assert tied <= max(1, B * n_kv // 8)
 
 
+@pytest.mark.parametrize("n_q,n_kv,G,k_budget", [(37, 1, 4, 128), (1999, 8, 4, 192), (2731, 8, 4, 128),
+                                                 (8209, 8, 8, 256)])
+def test_prefill_query_rotation_matches_fp32_products(n_q, n_kv, G, k_budget):
+    """bf16 queries on a 16-byte aligned buffer (exact bf16 products, both
+    workgroup sizes and the several passes of a large call, partial last
+    wave) against the same queries four bytes off (fp32 products).  The rotated
+    queries agree to fp32 rounding, so an output differs by at most what one
+    fp16 rounding of every softmax weight gives, 2^-11."""
+    bg = bgm()
+    st = P.make_setup(90, 1, 1, n_kv, G, (n_q + 63) // 64 * 64, k_budget, 2, 5e5, "bf16")
+    layout, cache = build(st)
+    g = torch.Generator(device="cuda").manual_seed(n_q)
+    K, V = (torch.randn((1, n_q, n_kv, 128), generator=g, device="cuda").bfloat16() for _ in range(2))
+    at = torch.zeros(1, dtype=torch.int32, device="cuda")
+    bg.blockgtq_quantize_append(st.cfg, layout, 0, K, V, at, cache, host_write_pos=[0])
+    q = torch.randn((1, n_q, n_kv * G, 128), generator=g, device="cuda").bfloat16()
+    off = torch.empty(q.numel() + 2, dtype=q.dtype, device="cuda")[2:].view(q.shape)
+    off.copy_(q)
+    assert q.data_ptr() % 16 == 0 and off.data_ptr() % 16 == 4
+    a, b = (bg.blockgtq_prefill_attn(st.cfg, layout, 0, x, at, n_q - 1, cache).double() for x in (q, off))
+    assert bool(torch.isfinite(a).all())
+    err = float((a - b).norm() / b.norm())
+    log(f"query rotation n_q {n_q} n_kv {n_kv} G {G}: {err:.1e}")
+    assert err <= 2.0 ** -11
+
+
 def test_uniform_k2_decode_many_positions():
     """Decode over a uniform K2 layout (one 2-bit group holding the whole
     key), the layout where the dropped lo part of the query matters most:
