@@ -201,8 +201,8 @@ __global__ __launch_bounds__(kThreads) void k_prefill_qrot(Dims d, const uint8_t
 // 4-wave workgroups for calls of up to 64K rows, which then spread over more
 // CUs.  The traffic bounds it (256 B in, 512 B out per row).
 // 32768 positions x 32 heads: the whole call 16.94 ms with fp32 products
-// (a 2-byte gather through LDS, 1.1 ms or more of it), 15.39 ms here; 1001
-// positions x 16 heads after 15003 rows: 575 and 466 us.
+// (a 2-byte gather through LDS), 15.26 ms here, the rotation itself 1.13 and
+// 0.18 ms (4.5 TB/s); 1001 positions x 16 heads after 15003 rows: 575 and 464 us.
 template <int W>
 __global__ __launch_bounds__(W * 64) void k_prefill_qrot_bf16(Dims d, const uint8_t* __restrict__ blob,
                                                               const void* __restrict__ q, int n_q, int iters,
