@@ -49,6 +49,7 @@
 
 #include "kernels.h"
 #include "layout.h"
+#include "mix.h"
 
 namespace bgtq {
 namespace split_detail {
@@ -75,14 +76,6 @@ __device__ __forceinline__ float opaque_nan() {
   uint32_t b = 0x7FC00000u;
   asm volatile("" : "+v"(b));
   return __uint_as_float(b);
-}
-// fp16(p0 lo(w)) | fp16(p1 hi(w)) << 16, w = two fp16: one mixed-precision
-// fused product into each half (single rounding to fp16)
-__device__ __forceinline__ uint32_t mix_pair(float p0, float p1, uint32_t w) {
-  uint32_t r;
-  asm("v_fma_mixlo_f16 %0, %1, %2, 0 op_sel_hi:[0,1,0]" : "=v"(r) : "v"(p0), "v"(w));
-  asm("v_fma_mixhi_f16 %0, %1, %2, 0 op_sel:[0,1,0] op_sel_hi:[0,1,0]" : "+v"(r) : "v"(p1), "v"(w));
-  return r;
 }
 
 // LDS map (bytes).  The b = 2 table has 32 replicas at a 256-byte entry

@@ -26,6 +26,7 @@
 
 #include "kernels.h"
 #include "layout.h"
+#include "mix.h"
 #include "split.h"
 
 namespace bgtq {
@@ -96,14 +97,6 @@ __device__ __forceinline__ float sum2g(float v) {
   float a, b;
   swap32(v, a, b);
   return a + b;
-}
-// fp16(p0 lo(w)) | fp16(p1 hi(w)) << 16, w = two fp16: one mixed-precision
-// product into each half (single rounding to fp16)
-__device__ __forceinline__ uint32_t mix_pair(float p0, float p1, uint32_t w) {
-  uint32_t r;
-  asm("v_fma_mixlo_f16 %0, %1, %2, 0 op_sel_hi:[0,1,0]" : "=v"(r) : "v"(p0), "v"(w));
-  asm("v_fma_mixhi_f16 %0, %1, %2, 0 op_sel:[0,1,0] op_sel_hi:[0,1,0]" : "+v"(r) : "v"(p1), "v"(w));
-  return r;
 }
 
 __device__ __forceinline__ float ld_q(const void* q, size_t i, int in_dtype) {  // BGTQ_BF16 = 1
