@@ -260,11 +260,12 @@ def test_prefill_attention_tile_edges(k_budget, v_bits, G, n_kv, n_q, pos0, dtyp
     up in pairs up to 6), G = 1 to 8, single-row tails, start positions on and
     off a tile, and both workgroup shapes (the last case has more than 256
     workgroups of 128 rows).  Every head at the positions around the tile and
-    workgroup edges, against the oracle within 2e-3.  A head in which a
-    coordinate lies within rounding of a decision threshold (the tie bound of
-    compare_codes) may hold another code there, which moves its logits by a
-    whole quantization step: its attention is not compared (at most one head in
-    eight)."""
+    workgroup edges, against the oracle within 2e-3.  A coordinate within
+    rounding of a decision threshold (the tie bound of compare_codes) may hold
+    another code than the oracle's, which moves every logit of its token by up
+    to a whole quantization step: a head is compared at the positions before its
+    first such token.  At least half of a case's heads (the head, where a case
+    has one) have no such token and are compared whole."""
     bg = bgm()
     total = [p + n_q for p in pos0]
     T, B = max(total), len(pos0)
@@ -278,32 +279,32 @@ def test_prefill_attention_tile_edges(k_budget, v_bits, G, n_kv, n_q, pos0, dtyp
     out = bg.blockgtq_prefill_attn(st.cfg, layout, 0, to_dev(q, dtype),
                                    torch.tensor(pos0, dtype=torch.int32, device="cuda"), T - 1, cache)
     out = out.cpu().numpy().astype(np.float64)
-    worst, stats, tied = 0.0, P.Stats(), 0
+    worst, stats, whole = 0.0, P.Stats(), 0
     for b in range(B):
         rows_per = max(1, 128 // G)
         want = {0, 1, n_q - 1, n_q // 2} | {e + d for e in range(rows_per, n_q, 4 * rows_per) for d in (-1, 0, 1)}
         want |= {64 * m - pos0[b] + d for m in (1, 2, 5) for d in (-1, 0)}
-        at = np.array(sorted(i for i in want if 0 <= i < n_q))
+        at_all = np.array(sorted(i for i in want if 0 <= i < n_q))
         for h in range(n_kv):
             rows = P.oracle_rows(st, 0, h, kv[b, h][0], kv[b, h][1])
-            before = stats.code_ties
             widths = P.stream_widths(st.bits[0, h])
-            kw = cache.k_codes[0, b, h, :T].cpu().numpy().view(np.uint32)
-            P.compare_codes(P.read_fields(kw, widths), rows.kcodes, rows.kz, widths, P.group_dims(st.bits[0, h]), stats)
-            vw = cache.v_codes[0, b, h].cpu().numpy().view(np.uint32)
-            P.compare_codes(P.read_value_codes(vw, v_bits, T), rows.vcodes, rows.vz, [v_bits] * 128,
-                            np.full(128, 128), stats)
-            if stats.code_ties > before:
-                tied += 1
+            kcodes = P.read_fields(cache.k_codes[0, b, h, :T].cpu().numpy().view(np.uint32), widths)
+            P.compare_codes(kcodes, rows.kcodes, rows.kz, widths, P.group_dims(st.bits[0, h]), stats)
+            vcodes = P.read_value_codes(cache.v_codes[0, b, h].cpu().numpy().view(np.uint32), v_bits, T)
+            P.compare_codes(vcodes, rows.vcodes, rows.vz, [v_bits] * 128, np.full(128, 128), stats)
+            tied = np.nonzero((kcodes != rows.kcodes).any(axis=1) | (vcodes != rows.vcodes).any(axis=1))[0]
+            whole += tied.size == 0
+            at = at_all if tied.size == 0 else at_all[pos0[b] + at_all < tied[0]]
+            if at.size == 0:
                 continue
             kh = o.dequantize_keys(rows.kcodes, rows.knorms, st.bits_oracle[0, h], st.rot_k)
             vh = o.dequantize_values(rows.vcodes, rows.vnorms, st.rot_v, v_bits)
             qq = q[b, at, h * G:(h + 1) * G].reshape(-1, 128)
             ref = o.prefill_attention(qq, np.repeat(pos0[b] + at, G), kh, vh)
             worst = max(worst, P.rel_err(out[b, at, h * G:(h + 1) * G].reshape(-1, 128), ref))
-    log("prefill edges max rel err", worst, "tied heads", tied)
+    log("prefill edges max rel err", worst, "heads compared whole", whole, "of", B * n_kv)
+    assert whole >= (B * n_kv + 1) // 2
     assert worst <= 2e-3
-    assert tied <= max(1, B * n_kv // 8)
 
 
 @pytest.mark.parametrize("n_q,n_kv,G,k_budget", [(37, 1, 4, 128), (1999, 8, 4, 192), (2731, 8, 4, 128),
