@@ -3,6 +3,7 @@
 Codes and norms: bit-exact except counted decision-boundary ties.
 Attention: max over (sequence, query head) of ||o_gpu - o_ref||_inf / ||o_ref||_inf <= 2e-3.
 """
+import math
 import sys
 
 import numpy as np
@@ -312,9 +313,20 @@ def test_prefill_attention_tile_edges(k_budget, v_bits, G, n_kv, n_q, pos0, dtyp
 def test_prefill_query_rotation_matches_fp32_products(n_q, n_kv, G, k_budget):
     """bf16 queries on a 16-byte aligned buffer (exact bf16 products, both
     workgroup sizes and the several passes of a large call, partial last
-    wave) against the same queries four bytes off (fp32 products).  The rotated
-    queries agree to fp32 rounding, so an output differs by at most what one
-    fp16 rounding of every softmax weight gives, 2^-11."""
+    wave) against the same queries four bytes off (fp32 products), row by row.
+
+    Rotated queries (the fp32 rows that the call leaves in its workspace): both
+    sides sum 128 products of one orthonormal rotation row and x in fp32, in
+    different orders, scaled by at most log2 e / 16 (a group has two dims or
+    more).  One rounding of 2^-23 per term on either side (an MFMA may truncate)
+    and the Cauchy-Schwarz bound of the sum give 2 * 128 * 2^-23 * log2 e / 16 *
+    |x| per element, 2.8e-6 of |x|.
+
+    Outputs: the logits (base 2) differ by at most ds = |difference of the
+    rotated query| |k|, a weight by 2 ds ln 2 of it (numerator and sum) and one
+    fp16 step, 2^-10 of it, and a row by as much of its weighted mean of |v|, at
+    most the largest stored |v|.  Stored keys and values are up to a quarter
+    longer than the given ones."""
     bg = bgm()
     st = P.make_setup(90, 1, 1, n_kv, G, (n_q + 63) // 64 * 64, k_budget, 2, 5e5, "bf16")
     layout, cache = build(st)
@@ -326,11 +338,19 @@ def test_prefill_query_rotation_matches_fp32_products(n_q, n_kv, G, k_budget):
     off = torch.empty(q.numel() + 2, dtype=q.dtype, device="cuda")[2:].view(q.shape)
     off.copy_(q)
     assert q.data_ptr() % 16 == 0 and off.data_ptr() % 16 == 4
-    a, b = (bg.blockgtq_prefill_attn(st.cfg, layout, 0, x, at, n_q - 1, cache).double() for x in (q, off))
-    assert bool(torch.isfinite(a).all())
-    err = float((a - b).norm() / b.norm())
-    log(f"query rotation n_q {n_q} n_kv {n_kv} G {G}: {err:.1e}")
-    assert err <= 2.0 ** -11
+    ws = [torch.empty(bg.prefill_workspace_bytes(st.cfg, n_q), dtype=torch.uint8, device="cuda") for _ in range(2)]
+    a, b = (bg.blockgtq_prefill_attn(st.cfg, layout, 0, x, at, n_q - 1, cache, workspace=w)
+            for x, w in zip((q, off), ws))
+    ra, rb = (w[:4 * q.numel()].view(torch.float32).view(q.shape) for w in ws)
+    assert bool(torch.isfinite(ra).all()) and bool(torch.isfinite(a).all())
+    limit = 2 * 128 * 2.0 ** -23 * math.log2(math.e) / 16
+    rot = float(((ra - rb).abs().amax(-1) / q.float().norm(dim=-1)).max())
+    kmax, vmax = (1.25 * float(x.float().norm(dim=-1).max()) for x in (K, V))
+    ds = float((ra - rb).norm(dim=-1).max()) * kmax
+    err = float((a - b).norm(dim=-1).max()) / vmax
+    log(f"query rotation n_q {n_q} n_kv {n_kv} G {G}: rotated rows {rot:.1e} of {limit:.1e}, outputs {err:.1e}, ds {ds:.1e}")
+    assert rot <= limit
+    assert err <= 2.0 ** -10 + 2 * ds * math.log(2)
 
 
 def test_uniform_k2_decode_many_positions():
