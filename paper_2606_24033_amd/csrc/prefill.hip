@@ -5,8 +5,9 @@
 // with a causal mask under an online softmax.  No fp16 cache and no attention
 // matrix is written.
 //
-// Three launches on the caller's stream:
-//  1. k_prefill_qrot: the Q-side rotation of every query row into the key
+// Two launches on the caller's stream:
+//  1. k_prefill_qrot_bf16 (bf16 queries on 16-byte aligned buffers) or
+//     k_prefill_qrot: the Q-side rotation of every query row into the key
 //     stream order, qr[p] = log2 e (Pi_g q_g)_j / sqrt(d_g d_h) at stream
 //     position p = g_pos[g] + j (fp32, into the caller's workspace);
 //  2. k_prefill_attn: the attention, 256 query rows per workgroup (8 waves of
@@ -20,8 +21,7 @@
 //     straight into the B operand of the PV product (no trip through LDS).
 //     The decoded tiles are double-buffered: while a tile's products run, the
 //     same waves decode the next tile into the other buffer; one barrier per
-//     tile;
-//  3. the same kernel's epilogue: out = Pi_V^T o, with fp32 MFMAs.
+//     tile.  Its epilogue: out = Pi_V^T o, with fp32 MFMAs.
 #include <hip/hip_runtime.h>
 
 #include "kernels.h"
@@ -77,8 +77,6 @@ template <class T>
 __device__ __forceinline__ T ld_at(const void* base, uint32_t byte_off) {
   return *reinterpret_cast<const T*>(static_cast<const char*>(base) + byte_off);
 }
-
-__device__ __forceinline__ float h2f(uint16_t b) { return static_cast<float>(__builtin_bit_cast(_Float16, b)); }
 
 // r0, r1 = the values of lanes l % 32 and l % 32 + 32 (the two lanes that hold
 // the same query row of an accumulator); gfx950 lane swap
@@ -193,9 +191,10 @@ __global__ __launch_bounds__(kThreads) void k_prefill_qrot(Dims d, const uint8_t
 // order folded in) and the scale applied to the sums.  A wave takes 32 rows;
 // 4-wave workgroups for calls of up to 64K rows, which then spread over more
 // CUs.  The traffic bounds it (256 B in, 512 B out per row).
-// 32768 positions x 32 heads: the whole call 16.94 ms with fp32 products
-// (a 2-byte gather through LDS), 15.26 ms here, the rotation itself 1.13 and
-// 0.18 ms (4.5 TB/s); 1001 positions x 16 heads after 15003 rows: 575 and 464 us.
+// Against fp32 products (a 2-byte gather through LDS), both in turn in one
+// run: 32768 positions x 32 heads 1.23 and 0.16 ms (5.0 TB/s), the attention
+// behind it 15.4 and 14.9 ms, the whole call 16.55 and 14.93 ms; 1001 positions
+// x 16 heads after 15003 rows, the call: 575 and 460 us.
 template <int W>
 __global__ __launch_bounds__(W * 64) void k_prefill_qrot_bf16(Dims d, const uint8_t* __restrict__ blob,
                                                               const void* __restrict__ q, int n_q, int iters,
@@ -400,13 +399,15 @@ __device__ __forceinline__ void store_values(uint8_t* dec, const Raw<BV>& raw, i
   reinterpret_cast<uint16_t*>(dec + kDecVN)[tid & 63] = static_cast<uint16_t>(raw.vn);
 }
 
-// What bounds it: per 64-token tile a SIMD's two waves issue 130 MFMAs of 32
-// cycles and about 600 VALU instructions, and one barrier; with everything but
-// the MFMAs taken out the 32K-token Llama-shaped layer takes 9.2 ms, measured
-// 15.2 ms (23.0 ms with 16x16x32 products and a per-code decode through raw
-// words in LDS): the waves' softmax and decode phases are only partly hidden
-// behind each other's products.  Three passes of the key product and the one
-// of the value product make 17.6 TFLOP of matrix work, 1.16 PFLOP/s.
+// What bounds it: per 64-token tile a SIMD's two waves issue 128 MFMAs of 32
+// cycles and 570 other VALU instructions, and meet at one barrier.  On the
+// 32K-token Llama-shaped layer (14.9 ms; 23.0 ms with 16x16x32 products and a
+// per-code decode through raw words in LDS) the matrix cores are busy 61 % of
+// the cycles and the VALU port 52 %; with the softmax and the decode taken out
+// (the products, their LDS reads and the barrier stay) it takes 11.5 ms.  The
+// waves' softmax and decode phases are only partly hidden behind each other's
+// products.  Three passes of the key product and the one of the value product
+// make 17.6 TFLOP of matrix work, 1.18 PFLOP/s.
 // Tried and slower or equal: two barriers per tile with the halves in
 // alternate phases (19.0 ms), the decode spread between the products (18.2),
 // four waves of 64 rows, one per SIMD (spills), 32-token blocks (16.4).
@@ -467,7 +468,10 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2,
   }
   const KeyItems items = key_items(M, wave, kw);
   // codebooks and pair tables (entry i of width b holds the centroids of codes
-  // i % 2^b and i / 2^b)
+  // i % 2^b and i / 2^b), of every width: 5460 entries.  Calls of a tile or a
+  // few carry that and are still shorter than with the per-code decode, which
+  // needed no tables: one position 27 against 42 us the call, 64 positions 30
+  // against 82 us, 64 sequences of 16 positions 71 against 105 us (8 KV heads x 4).
   {
     const uint16_t* c16 = reinterpret_cast<const uint16_t*>(blob + kOffC16);
     uint16_t* cbs = reinterpret_cast<uint16_t*>(smem + kOffCb);
@@ -564,7 +568,6 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2,
       for (int i = 0; i < 16; ++i) s[n][i] = 0.f;
     read_keys(0);
     read_keys(1);
-    
 #pragma unroll
     for (int u = 0; u < 8 * NB; ++u) {
       if (u + 2 < 8 * NB) read_keys(u + 2);
@@ -575,7 +578,6 @@ __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2,
       s[n] = __builtin_amdgcn_mfma_f32_32x32x16_f16(ka[u % 3][0], ql[ks], s[n], 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
-    
   };
 
   // Causal mask and online softmax (base 2) of tile kt, then O^T += V^T P^T.
@@ -777,10 +779,10 @@ hipError_t launch_attn(const Dims& d, const uint8_t* blob, const float* qr, int 
   };
   // 128-row workgroups while they all fit the 256 CUs at once: half the rows
   // take half the time per tile (1001 positions x 8 heads x 2 KV heads after
-  // 15003 rows: 0.58 against 0.68 ms).  Above that every tile would be decoded
+  // 15003 rows: 0.46 against 0.70 ms).  Above that every tile would be decoded
   // twice as often for the same products (2048 positions x 4 heads x 8 KV
-  // heads: 0.29 against 0.25 ms with 256 rows; 32768 positions: 19.5 against
-  // 16.3 ms).
+  // heads: 0.19 against 0.15 ms with 256 rows; 32768 positions: 17.2 against
+  // 14.7 ms).
   constexpr int rows1 = kAttnWaves * kWaveRows, rows2 = rows1 / 2;
   if ((nr + rows2 - 1) / rows2 * d.n_kv * d.batch <= 256) go(k_prefill_attn<BV, 2>, rows2);
   else go(k_prefill_attn<BV, 1>, rows1);
@@ -803,6 +805,13 @@ hipError_t launch_prefill_attn(const Dims& d, const void* layout, const void* q,
       hipLaunchKernelGGL(kern, dim3((nr + per - 1) / per, d.n_kv, d.batch), dim3(w * 64), 0, s, d, blob, q, n_q, iters,
                          qr_ws);
     };
+    // 4-wave workgroups up to 64K rows, where 16-wave ones would leave CUs
+    // idle; above, 16 waves share one staging of the matrix, and above 512K rows
+    // four passes of the workgroup do.  us of the rotation with 4 waves / 16
+    // waves / 16 waves and four passes: 16K rows 11 / 16 / 44, 32K 16 / 19 / 48,
+    // 64K 22 / 18 / 45, 96K 28 / 18 / 45, 512K 171 / 106 / 90, 640K 198 / 119 /
+    // 159, 1M 308 / 212 / 172 (the true crossings lie near 48K and, by whole
+    // rounds of workgroups, between 256K and 1M rows).
     if (rows <= 256L * 256) go(k_prefill_qrot_bf16<4>, 4, 1);
     else go(k_prefill_qrot_bf16<16>, 16, rows <= 4L * 256 * 512 ? 1 : 4);
   } else {
