@@ -43,7 +43,7 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 FP32_PEAK_TFLOPS = 157.3
 F16_MFMA_PEAK_TFLOPS = 2500.0
-KERNEL_SRC = os.path.join(ROOT, "paper_2606_24033_amd", "csrc", "decode_impl.h")
+KERNEL_SRCS = [os.path.join(ROOT, "paper_2606_24033_amd", "csrc", f) for f in ("decode_impl.h", "mix.h")]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_split_mfma_llama8b_128k_k2v2_traffic.json")
 N_SINK, N_RECENT = 4, 128      # protected-buffer regime of the reasoning evaluation
 N_CAL = 2048
@@ -90,8 +90,11 @@ def parse():
 
 
 def kernel_sha():
-    with open(KERNEL_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    h = hashlib.sha256()
+    for path in KERNEL_SRCS:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()
 
 
 def measured_traffic():
@@ -576,7 +579,7 @@ def prefill_measurement(bg, synth, torch, m, T):
            "ms_per_call": round(ms, 3), "algorithmic_tflops": round(flops / ms / 1e9, 1),
            "roofline": {"bound": "mfma", "achieved": round(flops / ms / 1e9, 1), "peak": F16_MFMA_PEAK_TFLOPS,
                         "unit": "TFLOP/s", "frac": round(flops / ms / 1e9 / F16_MFMA_PEAK_TFLOPS, 4),
-                        "flops_per_call": flops, "kernel": "k_prefill_qrot + k_prefill_attn"}}
+                        "flops_per_call": flops, "kernel": "k_prefill_qrot_bf16 + k_prefill_attn"}}
     try:
         k16 = k.half().transpose(0, 1)[None].repeat_interleave(m.G, dim=1).contiguous()
         v16 = v.half().transpose(0, 1)[None].repeat_interleave(m.G, dim=1).contiguous()
